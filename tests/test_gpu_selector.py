@@ -187,6 +187,20 @@ def test_exact_ties_pick_the_lowest_id():
     run_case(B, L, V, mask_id, logits, mask.clone(), prev.clone(), sps)
 
 
+@pytest.mark.parametrize("B,L", [(2, 33), (9, 130)])          # few rows: 1024 threads each; over 1024 rows: 256
+@pytest.mark.parametrize("V", [3, 9, 1003, 8203])              # rows start at every 2-byte offset, no whole chunk to several rounds
+@pytest.mark.parametrize("mask_at", ["first", "last"])
+def test_rows_that_start_between_16_byte_boundaries(B, L, V, mask_at):
+    """Ids in front of a row's first 16-byte boundary, in whole chunks and behind the last boundary: values from a
+    handful, so that nearly every row's maximum is tied across those regions and the lowest id has to win."""
+    g = torch.Generator().manual_seed(V + B)
+    logits = torch.randint(-2, 3, (B, L, V), generator=g).to(torch.bfloat16)
+    mask = (torch.rand((B, L), generator=g) < 0.7).to(torch.uint8)
+    prev = torch.randint(0, V, (B, L), generator=g).to(torch.int32)
+    sps = [sf.StageParams(sf.SLOW, 0, 0, 2, 0.1, 0.9, 0, 0, L) for _ in range(B)]
+    run_case(B, L, V, 0 if mask_at == "first" else V - 1, logits, mask, prev, sps)
+
+
 def test_mask_id_is_never_predicted():
     B, L, V = 1, 12, 2048
     logits, mask, prev, mask_id = make_inputs("selector", B, L, V, seed_shift=5)
