@@ -458,39 +458,45 @@ __device__ __forceinline__ void residual_tile(floatx16 (&acc)[TM][TN], const flo
     }
 }
 
+// Called by every thread of a kEpiResidual workgroup after it has written its partial tile to its slab: takes a
+// ticket and says whether this split is the last of its tile to arrive (the others are done).  No workgroup waits
+// for another.  One thread publishes for the workgroup: the barrier orders every thread's slab stores before its
+// device-scope release (a single write-back of the L2 per workgroup instead of one per wave), the ticket is taken,
+// and only the workgroup that finds itself last pays for the acquire (which drops what its L2 holds of other
+// workgroups' lines).  The second barrier hands the result to the others.
+__device__ __forceinline__ bool last_split_of_tile(const RopeArgs &ea)
+{
+    __shared__ int s_ticket;
+    const int splits = gridDim.y;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        const int t = __hip_atomic_fetch_add(&ea.tickets[blockIdx.x], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (t == splits - 1) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            ea.tickets[blockIdx.x] = 0;    // ready for the next launch; nobody else looks at it any more
+        }
+        s_ticket = t;
+    }
+    __syncthreads();
+    return s_ticket == splits - 1;         // uniform over the workgroup
+}
+
 // The tail of a kEpiResidual workgroup: with one K split the accumulators are the whole product; with more,
-// every split leaves its partial tile in its slab and takes a ticket, and the split that takes the last ticket
-// of a tile adds everything up (the others are done).  No workgroup waits for another.
+// every split leaves its partial tile in its slab, and the last one to arrive adds everything up.
 template <int TM, int TN, int WTM, int WN>
 __device__ __forceinline__ void residual_finish(floatx16 (&acc)[TM][TN], void *slabs, int M, int N, int m0, int n0, int wm,
                                                 int wn, int l32, int lhalf, int pid_n, const RopeArgs &ea)
 {
-    __shared__ int s_ticket;
-    const int splits = gridDim.y, my_split = blockIdx.y;
+    const int splits = gridDim.y;
     if (splits > 1) {
-        store_tile<TM, TN, WTM, kEpiPartial, true>(acc, slabs, M, N, m0, n0, wm, wn, l32, lhalf, my_split, ea);
-        // One thread publishes for the workgroup: the barrier orders every thread's slab stores before its
-        // device-scope release (a single write-back of the L2 per workgroup instead of one per wave), the
-        // ticket is taken, and only the workgroup that finds itself last pays for the acquire (which drops
-        // what its L2 holds of other workgroups' lines).  The second barrier hands the result to the others.
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-            const int t = __hip_atomic_fetch_add(&ea.tickets[blockIdx.x], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (t == splits - 1) {
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-                ea.tickets[blockIdx.x] = 0;    // ready for the next launch; nobody else looks at it any more
-            }
-            s_ticket = t;
-        }
-        __syncthreads();
-        if (s_ticket != splits - 1) return;    // uniform over the workgroup
-    }
-    if (splits > 1)
+        store_tile<TM, TN, WTM, kEpiPartial, true>(acc, slabs, M, N, m0, n0, wm, wn, l32, lhalf, blockIdx.y, ea);
+        if (!last_split_of_tile(ea)) return;
         residual_tile<TM, TN, WTM, true>(acc, reinterpret_cast<const float *>(slabs), splits, M, N, m0, n0, wm, wn, l32, lhalf,
                                          pid_n * WN + wn, ea);
-    else
+    } else {
         residual_tile<TM, TN, WTM, false>(acc, nullptr, 1, M, N, m0, n0, wm, wn, l32, lhalf, pid_n * WN + wn, ea);
+    }
 }
 
 // RowScale: the factors of the workgroup's BM rows, rsqrt(mean square + eps) from the partial sums of squares
@@ -707,6 +713,442 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_il_kernel(const uint16_t *_
     store_tile<TM, TN, WTM, EPI, true>(acc, Cout, M, N, m0, n0, wm, wn, l32, lhalf, blockIdx.y, rope, inv);
 }
 
+// ---- epilogues of the 16x16 tiles --------------------------------------------------
+// Element e of lane l of a transposed 16x16 tile is output row l % 16, tile column 4 (l / 16) + e.  Paired
+// epilogues: tile 2 s holds the first partners of 16 pairs and tile 2 s + 1 the second ones (w_global_row).
+template <int TM, int TN, int WTM, int EPI, bool GUARD>
+__device__ __forceinline__ void store_tile16(floatx4 (&acc)[TM][TN], void *Cout, int M, int N, int m0, int n0, int wm, int wn,
+                                             int lane, int split, const RopeArgs &rope, const float *s_inv)
+{
+    const int r16 = lane & 15, g4 = lane >> 4;
+    if constexpr (EPI == kEpiRowStats) {
+        // planes [parts][M] as in store_tile; the slice of this wave is part n0 / (16 TN) + wn
+        constexpr float kLog2e = 1.4426950408889634f, kNegBig = -3.0e38f;
+        const size_t plane = (size_t)rope.parts * M;
+        float *pm = reinterpret_cast<float *>(Cout) + (size_t)(n0 / (16 * TN) + wn) * M;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int row = m0 + wm * WTM + i * 16 + r16;
+            const float inv = s_inv ? s_inv[wm * WTM + i * 16 + r16] : 1.0f;
+            float m = kNegBig;
+            int c = 0x7fffffff;
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int col = n0 + (wn * TN + j) * 16 + 4 * g4;
+                const uint32_t w01 = pack_bf16x2(acc[i][j][0] * inv, acc[i][j][1] * inv);
+                const uint32_t w23 = pack_bf16x2(acc[i][j][2] * inv, acc[i][j][3] * inv);
+                const float x[4] = {__uint_as_float(w01 << 16), __uint_as_float(w01 & 0xffff0000u),
+                                    __uint_as_float(w23 << 16), __uint_as_float(w23 & 0xffff0000u)};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const bool legal = col + e < N && col + e != rope.mask_id;
+                    const float v = legal ? x[e] : -INFINITY;
+                    acc[i][j][e] = v;
+                    if (v > m) {  // columns are visited in increasing order: the first maximum stays
+                        m = v;
+                        c = col + e;
+                    }
+                }
+            }
+            const float off = -m * kLog2e;
+            float s = 0.0f;
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s += __builtin_amdgcn_exp2f(fmaf(acc[i][j][e], kLog2e, off));
+            s = m > kNegBig ? s : 0.0f;
+            // the other quarters of the row's columns sit in lanes ^ 16, ^ 32
+#pragma unroll
+            for (int o = 16; o <= 32; o <<= 1) {
+                const float m2 = __shfl_xor(m, o, 64), s2 = __shfl_xor(s, o, 64);
+                const int c2 = __shfl_xor(c, o, 64);
+                const float mt = fmaxf(m, m2);
+                s = s * __builtin_amdgcn_exp2f((m - mt) * kLog2e) + s2 * __builtin_amdgcn_exp2f((m2 - mt) * kLog2e);
+                c = (m > m2 || (m == m2 && c < c2)) ? c : c2;
+                m = mt;
+            }
+            if (g4 == 0 && row < M) {
+                pm[row] = m;
+                pm[plane + row] = s;
+                reinterpret_cast<int *>(pm)[2 * plane + row] = c;
+            }
+        }
+    } else if constexpr (EPI == kEpiSwiglu) {
+        uint16_t *C = reinterpret_cast<uint16_t *>(Cout);
+        const int n_out = N / 2;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int row = m0 + wm * WTM + i * 16 + r16;
+            const float inv = s_inv ? s_inv[wm * WTM + i * 16 + r16] : 1.0f;
+#pragma unroll
+            for (int s = 0; s < TN / 2; ++s) {
+                const int col = n0 + (wn * (TN / 2) + s) * 16 + 4 * g4;
+                float y[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float g = acc[i][2 * s][e] * inv, u = acc[i][2 * s + 1][e] * inv;
+                    y[e] = g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;  // 1 ulp reciprocal, far below the bf16 rounding
+                }
+                if (GUARD && (row >= M || col >= n_out)) continue;
+                // panel-major: element (row, col) sits at ((col / 32) * panel_rows + row) * 32 + col % 32
+                uint16_t *p = rope.c_panel_rows ? C + ((size_t)(col >> 5) * rope.c_panel_rows + row) * 32 + (col & 31)
+                                                : C + (size_t)row * n_out + col;
+                if (!GUARD || (col + 3 < n_out && (n_out & 3) == 0)) {
+                    uint2 w;
+                    w.x = pack_bf16x2(y[0], y[1]);
+                    w.y = pack_bf16x2(y[2], y[3]);
+                    *reinterpret_cast<uint2 *>(p) = w;
+                } else {
+                    for (int e = 0; e < 4 && col + e < n_out; ++e) p[e] = float_to_bf16_bits(y[e]);
+                }
+            }
+        }
+    } else if constexpr (EPI == kEpiRope64 || EPI == kEpiRope128) {
+        constexpr int HD = epi_head_dim(EPI) / 2;
+        uint16_t *C = reinterpret_cast<uint16_t *>(Cout);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int row = m0 + wm * WTM + i * 16 + r16;
+            const float2 *trow = rope.table + (size_t)(rope.pos ? rope.pos[min(row, M - 1)] : row % rope.L) * HD;
+            const float inv = s_inv ? s_inv[wm * WTM + i * 16 + r16] : 1.0f;
+            // keys and values of a gathered row go straight to the row's place in the cache
+            uint16_t *crow = C + (size_t)row * N;
+            uint16_t *kvrow = rope.kv_dst ? rope.kv_dst + (size_t)rope.kv_rows[min(row, M - 1)] * N : crow;
+            const int kv_first = N / 3;
+#pragma unroll
+            for (int s = 0; s < TN / 2; ++s) {
+                const int p = n0 + (wn * (TN / 2) + s) * 16 + 4 * g4;  // first of the lane's 4 pairs
+                const int pp = p % HD, col = (p / HD) * (2 * HD) + pp;
+                if (GUARD && (row >= M || p >= N / 2)) continue;
+                float a[4], b[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    a[e] = acc[i][2 * s][e] * inv;
+                    b[e] = acc[i][2 * s + 1][e] * inv;
+                }
+                if (col < rope.rope_cols) {
+                    const float4 *tp = reinterpret_cast<const float4 *>(trow + pp);  // 4 (cos, sin) pairs
+                    const float4 t01 = tp[0], t23 = tp[1];
+                    const float cs[4] = {t01.x, t01.z, t23.x, t23.z}, sn[4] = {t01.y, t01.w, t23.y, t23.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float x = a[e], y = b[e];
+                        a[e] = x * cs[e] - y * sn[e];
+                        b[e] = x * sn[e] + y * cs[e];
+                    }
+                }
+                uint16_t *dst = (col >= kv_first ? kvrow : crow) + col;   // (a pair never straddles two thirds)
+                uint2 w;
+                w.x = pack_bf16x2(a[0], a[1]);
+                w.y = pack_bf16x2(a[2], a[3]);
+                *reinterpret_cast<uint2 *>(dst) = w;
+                w.x = pack_bf16x2(b[0], b[1]);
+                w.y = pack_bf16x2(b[2], b[3]);
+                *reinterpret_cast<uint2 *>(dst + HD) = w;
+            }
+        }
+    } else if constexpr (EPI == kEpiBf16) {
+        uint16_t *C = reinterpret_cast<uint16_t *>(Cout);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int row = m0 + wm * WTM + i * 16 + r16;
+            const float inv = s_inv ? s_inv[wm * WTM + i * 16 + r16] : 1.0f;
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int col = n0 + (wn * TN + j) * 16 + 4 * g4;
+                if (GUARD && (row >= M || col >= N)) continue;
+                uint16_t *p = C + (size_t)row * N + col;
+                if (!GUARD || (col + 3 < N && (N & 3) == 0)) {
+                    uint2 w;
+                    w.x = pack_bf16x2(acc[i][j][0] * inv, acc[i][j][1] * inv);
+                    w.y = pack_bf16x2(acc[i][j][2] * inv, acc[i][j][3] * inv);
+                    *reinterpret_cast<uint2 *>(p) = w;
+                } else {
+                    for (int e = 0; e < 4 && col + e < N; ++e) p[e] = float_to_bf16_bits(acc[i][j][e] * inv);
+                }
+            }
+        }
+    } else {
+        float *C = reinterpret_cast<float *>(Cout) + (size_t)split * M * N;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int row = m0 + wm * WTM + i * 16 + r16;
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int col = n0 + (wn * TN + j) * 16 + 4 * g4;
+                if (GUARD && (row >= M || col >= N)) continue;
+                float *p = C + (size_t)row * N + col;
+                if (!GUARD || (col + 3 < N && (N & 3) == 0)) {
+                    *reinterpret_cast<float4 *>(p) = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+                } else {
+                    for (int e = 0; e < 4 && col + e < N; ++e) p[e] = acc[i][j][e];
+                }
+            }
+        }
+    }
+}
+
+// residual_tile for the 16x16 layout (same outputs, same order of the sums inside an element)
+template <int TM, int TN, int WTM, bool FROM_SLABS>
+__device__ __forceinline__ void residual_tile16(floatx4 (&acc)[TM][TN], const float *slabs, int splits, int M, int N, int m0,
+                                                int n0, int wm, int wn, int lane, int part, const RopeArgs &ea)
+{
+    const size_t slab = (size_t)M * N;
+    const int r16 = lane & 15, g4 = lane >> 4;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int row = m0 + wm * WTM + i * 16 + r16;
+        float ss = 0.0f;
+        float4 v[TN];
+        bool ok[TN];
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int col = n0 + (wn * TN + j) * 16 + 4 * g4;
+            ok[j] = row < M && col < N;                       // (N % 4 == 0: checked by the host)
+            v[j] = ok[j] ? *reinterpret_cast<const float4 *>(ea.x + (size_t)row * N + col) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        }
+        if constexpr (FROM_SLABS) {
+            for (int s = 0; s < splits; ++s) {
+                float4 p[TN];
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    const int col = n0 + (wn * TN + j) * 16 + 4 * g4;
+                    p[j] = ok[j] ? *reinterpret_cast<const float4 *>(slabs + s * slab + (size_t)row * N + col)
+                                 : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                }
+#pragma unroll
+                for (int j = 0; j < TN; ++j) { v[j].x += p[j].x; v[j].y += p[j].y; v[j].z += p[j].z; v[j].w += p[j].w; }
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < TN; ++j) { v[j].x += acc[i][j][0]; v[j].y += acc[i][j][1]; v[j].z += acc[i][j][2]; v[j].w += acc[i][j][3]; }
+        }
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            if (!ok[j]) continue;
+            const int col = n0 + (wn * TN + j) * 16 + 4 * g4;
+            const size_t at = (size_t)row * N + col;
+            const float4 t = v[j];
+            *reinterpret_cast<float4 *>(ea.x + at) = t;
+            ss += t.x * t.x + t.y * t.y + t.z * t.z + t.w * t.w;
+            const uint2 g = *reinterpret_cast<const uint2 *>(ea.gain + col);
+            uint2 o;
+            o.x = pack_bf16x2(t.x * bf16_lo(g.x), t.y * bf16_hi(g.x));
+            o.y = pack_bf16x2(t.z * bf16_lo(g.y), t.w * bf16_hi(g.y));
+            uint16_t *hp = ea.c_panel_rows ? ea.h_out + ((size_t)(col >> 5) * ea.c_panel_rows + row) * 32 + (col & 31)
+                                           : ea.h_out + at;
+            *reinterpret_cast<uint2 *>(hp) = o;
+        }
+        ss += __shfl_xor(ss, 16, 64);                               // the other quarters of the row's columns
+        ss += __shfl_xor(ss, 32, 64);
+        if (g4 == 0 && row < M) ea.ssq_out[(size_t)row * ea.ssq_out_stride + part] = ss;
+    }
+}
+
+// residual_finish for the 16x16 layout
+template <int BM, int BN, int TM, int TN, int WTM, int WN>
+__device__ __forceinline__ void residual_finish16(floatx4 (&acc)[TM][TN], void *slabs, int M, int N, int m0, int n0, int wm,
+                                                  int wn, int lane, int pid_n, const RopeArgs &ea)
+{
+    if constexpr (BM * BN < 256 * 256) {             // (never planned with splits on the largest tile)
+        if (gridDim.y > 1) {
+            store_tile16<TM, TN, WTM, kEpiPartial, true>(acc, slabs, M, N, m0, n0, wm, wn, lane, blockIdx.y, ea, nullptr);
+            if (!last_split_of_tile(ea)) return;
+            residual_tile16<TM, TN, WTM, true>(acc, reinterpret_cast<const float *>(slabs), gridDim.y, M, N, m0, n0, wm, wn, lane,
+                                               pid_n * WN + wn, ea);
+            return;
+        }
+    }
+    residual_tile16<TM, TN, WTM, false>(acc, nullptr, 1, M, N, m0, n0, wm, wn, lane, pid_n * WN + wn, ea);
+}
+
+// ---- 16x16x32 kernel: K % 64 == 0 ------------------------------------------------
+// acc += W fragment x A fragment, in place.  Inline asm because the compiler gives the builtin's result other
+// registers than its addend and then moves up to 200 accumulators per stage; the accumulators stay in AGPRs.
+// It does not see that this is a matrix instruction: nothing but another mfma16 may touch an accumulator before
+// mfma16_settle (the reader of a result has to keep a distance that the compiler inserts only for builtins), and
+// the operands come straight from LDS reads (one that a vector instruction wrote would need two idle states in
+// front, as in mfma16_zero; in front of every product they cost 15 % of the loop).
+__device__ __forceinline__ void mfma16(floatx4 &acc, bf16x8 w, bf16x8 a)
+{
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(a));
+}
+// (a product of zeros instead of register writes, for the same reason)
+template <int TM, int TN>
+__device__ __forceinline__ void mfma16_zero(floatx4 (&acc)[TM][TN])
+{
+    const bf16x8 z = as_bf16x8(make_uint4(0, 0, 0, 0));
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %1, 0" : "=a"(acc[i][j]) : "v"(z));
+}
+template <int TM, int TN>
+__device__ __forceinline__ void mfma16_settle(floatx4 (&acc)[TM][TN])
+{
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i][j]));   // no use of it moves above the wait
+}
+// Four waves of TM x TN 16x16 tiles, 32-deep stages in an LDS ring, one barrier per stage.  While the products of
+// stage k run on fragments in registers, the fragments of stage k + 1 are read (spread over the first three quarters
+// of the MFMAs) and stage k + NST is copied into the slot that stage k has left (copies spread over all of them).
+// Bound: power, and the LDS (reads and copies of a 256x256 tile take 75 % of its cycles).  Against 32x32x16 products
+// in gemm_il_kernel's order at 12288 rows, K = 4096, N = 24576 SwiGLU / 12288 rotary: 1940 -> 1775 us / 1045 -> 995 us,
+// K = 8192, N = 4096: 665 -> 597 us (1.38 PFLOP/s): a 16x16x32 product moves half the accumulator bytes per flop, and
+// a stage's reads stay ahead of its products by a whole stage.  Tile heights are multiples of 32, not of 64, so that
+// 160-row tiles hold 288 rows in two (SwiGLU, 288 rows: 79 -> 60 us) and 137 in one (55 -> 47 us).
+// Eight waves in two groups that take turns at reading and multiplying measured 1916 us: the narrower wave tiles
+// read 1.5 times as much LDS.
+template <int BM, int BN, int WM, int WN, int NST, int EPI>
+__global__ __launch_bounds__(WM * WN * 64) void gemm_q_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
+                                                              void *__restrict__ Cout, int M, int N, int K, int k_per_split,
+                                                              int num_m, int num_n, RopeArgs rope)
+{
+    constexpr int NW = WM * WN, BK = 32;
+    constexpr int WTM = BM / WM, WTN = BN / WN, TM = WTM / 16, TN = WTN / 16;
+    static_assert(TM >= 1 && TN >= 1 && WTM % 16 == 0 && WTN % 16 == 0, "wave tile is made of 16x16 MFMA tiles");
+    static_assert(!epi_paired(EPI) || WTN % 32 == 0, "pairs share a wave");
+    constexpr int CPR = BK / 8, RPI = 64 / CPR;    // 16-byte chunks per LDS row; rows moved by one copy instruction
+    // copy instructions of a stage: FULL per wave, and one more for the first REM waves
+    constexpr int ROWS = BM + BN, NI = ROWS / RPI, FULL = NI / NW, REM = NI % NW, LOADS = FULL + (REM ? 1 : 0), A_NI = BM / RPI;
+    static_assert(ROWS % RPI == 0 && BM % RPI == 0, "whole copy instructions");
+    constexpr bool kNtW = EPI == kEpiRowStats && A_NI % NW == 0;
+    static_assert(NST >= 3 && (NST - 1) * LOADS <= 63, "ring");
+    constexpr int STAGE = ROWS * CPR;
+    constexpr int NMF = TM * TN, NRD = TM + TN;
+    extern __shared__ uint4 smem[];
+
+    int pid_m, pid_n;
+    tile_of(blockIdx.x, num_m, num_n, pid_m, pid_n);
+    constexpr int BN_OUT = epi_paired(EPI) ? BN / 2 : BN;
+    const int m0 = pid_m * BM, n0 = pid_n * BN_OUT;
+    const int kbeg = blockIdx.y * k_per_split;
+    const int kend = min(K, kbeg + k_per_split);
+    const int nk = (kend - kbeg) / BK;             // even: K and the splits are multiples of 64
+
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int wm = wave / WN, wn = wave % WN;
+    const int l16 = lane & 15, g4 = lane >> 4;
+
+    const int lrow = lane / CPR, lslot = lane % CPR;
+    const bool extra = REM && wave < REM;
+    uint32_t goff[LOADS];  // byte offsets into A or W; rows past the edge are clamped
+#pragma unroll
+    for (int t = 0; t < LOADS; ++t) {
+        const int q = wave + NW * t, r = q * RPI + lrow;
+        const int grow = q < A_NI ? min(m0 + r, M - 1) : w_global_row<EPI>(min(r - BM, BN - 1), n0, N);
+        const int chunk = lslot ^ ((r >> 2) & 3);
+        goff[t] = (uint32_t)grow * (q < A_NI ? rope.a_row_pitch : rope.w_row_pitch) + chunk * 16;
+    }
+    const size_t a_stage = rope.a_panel_pitch, w_stage = rope.w_panel_pitch;
+    const char *Ab = reinterpret_cast<const char *>(A) + (size_t)(kbeg / 32) * a_stage;   // next stage to copy
+    const char *Wb = reinterpret_cast<const char *>(W) + (size_t)(kbeg / 32) * w_stage;
+    const uint32_t lds0 = lds_addr_of(smem) + wave * 1024;
+#define DLLM_COPY(t_, slot_off_)                                                                 \
+    do {                                                                                         \
+        if ((t_) >= FULL && !extra) break;                                                       \
+        const char *b_ = (wave + NW * (t_)) < A_NI ? Ab : Wb;                                    \
+        if (kNtW && (t_) >= A_NI / NW) async_load16<true>(b_, goff[t_], lds0 + (slot_off_) + (t_) * (NW * 1024)); \
+        else async_load16<false>(b_, goff[t_], lds0 + (slot_off_) + (t_) * (NW * 1024));         \
+    } while (0)
+
+    floatx4 acc[TM][TN];
+    // fragment: lane l holds row l % 16, K chunk l / 16 of a 16-row group (1 KB of LDS)
+    const int fo = l16 * CPR + (g4 ^ ((l16 >> 2) & 3));
+    const int a_base = wm * WTM * CPR + fo, b_base = (BM + wn * WTN) * CPR + fo;
+    bf16x8 af[2][TM], bfr[2][TN];
+#define DLLM_READ(ridx_, st_, buf_)                                                      \
+    do {                                                                                  \
+        if ((ridx_) < TN) bfr[buf_][(ridx_) % TN] = as_bf16x8((st_)[b_base + (ridx_) * 16 * CPR]);             \
+        else af[buf_][((ridx_) - TN) % TM] = as_bf16x8((st_)[a_base + ((ridx_) - TN) * 16 * CPR]); \
+    } while (0)
+
+    asm volatile("" ::"s"(Cout), "s"(M), "s"(N), "s"(rope.table), "s"(rope.pos), "s"(rope.L), "s"(rope.rope_cols),
+                 "s"(rope.c_panel_rows), "s"(rope.row_ssq), "s"(rope.x), "s"(rope.gain), "s"(rope.h_out), "s"(rope.ssq_out),
+                 "s"(rope.tickets), "s"(rope.ssq_out_stride));
+    __shared__ float s_inv[BM];
+    row_scale_prologue<BM>(s_inv, m0, M, K, rope);   // (its loads are complete before the first copy is issued)
+
+#pragma unroll
+    for (int s = 0; s < NST; ++s)
+        if (s < nk) {
+#pragma unroll
+            for (int t = 0; t < LOADS; ++t) DLLM_COPY(t, s * (STAGE * 16));
+            Ab += a_stage;
+            Wb += w_stage;
+        }
+    mfma16_zero<TM, TN>(acc);                         // while the first stage is on its way
+    if (extra) wait_stages_after<NST - 1, FULL + 1>(min(NST, nk) - 1);
+    else wait_stages_after<NST - 1, FULL>(min(NST, nk) - 1);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int r = 0; r < NRD; ++r) DLLM_READ(r, smem, 0);
+
+    int slot = 0;                                     // slot of stage k, free once its fragments are in registers
+    // one stage: multiplies the fragments of stage k (buffer U), reads those of stage k + 1 and, in the steady state or
+    // where such a stage exists, copies stage k + NST
+    auto step = [&](auto steady_tag, auto buf_tag, int k) __attribute__((always_inline)) {
+        constexpr bool STEADY = decltype(steady_tag)::value;
+        constexpr int cur = decltype(buf_tag)::value, nxt = cur ^ 1;
+        const int next_slot = slot + 1 == NST ? 0 : slot + 1;
+        const uint4 *stn = smem + next_slot * STAGE;
+        // every fragment of stage k is in registers, stage k + 1 has landed for this wave, and after the
+        // barrier both hold for all of them
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (STEADY && extra) wait_vmcnt<(NST - 2) * (FULL + 1)>();
+        else if (STEADY) wait_vmcnt<(NST - 2) * FULL>();
+        else if (extra) wait_stages_after<NST - 2, FULL + 1>(nk - 2 - k);
+        else wait_stages_after<NST - 2, FULL>(nk - 2 - k);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        const uint32_t slot_off = (uint32_t)slot * (STAGE * 16);
+        constexpr int RSPAN = NMF * 3 / 4 > NRD ? NMF * 3 / 4 : NMF;   // MFMAs the reads are spread over
+#pragma unroll
+        for (int m = 0; m < NMF; ++m) {
+            const int i = m / TN, j = m % TN;
+#pragma unroll
+            for (int r = 0; r < NRD; ++r)
+                if (r * RSPAN / NRD == m) DLLM_READ(r, stn, nxt);
+#pragma unroll
+            for (int c = 0; c < LOADS; ++c)
+                if (c * NMF / LOADS + (NMF / LOADS) / 2 == m && (STEADY || (NST & 1 && k + NST < nk))) DLLM_COPY(c, slot_off);
+            mfma16(acc[i][j], bfr[cur][j], af[cur][i]);
+            __builtin_amdgcn_sched_barrier(0);  // keeps the hand-made interleaving
+        }
+        Ab += a_stage;
+        Wb += w_stage;
+        slot = next_slot;
+    };
+    using std::integral_constant;
+    const int kt_steady = max(0, nk - NST) & ~1;
+    int kt = 0;
+    for (; kt < kt_steady; kt += 2) {
+        step(std::true_type{}, integral_constant<int, 0>{}, kt);
+        step(std::true_type{}, integral_constant<int, 1>{}, kt + 1);
+    }
+    for (; kt < nk; kt += 2) {
+        step(std::false_type{}, integral_constant<int, 0>{}, kt);
+        step(std::false_type{}, integral_constant<int, 1>{}, kt + 1);
+    }
+    mfma16_settle<TM, TN>(acc);
+#undef DLLM_COPY
+#undef DLLM_READ
+    if constexpr (EPI == kEpiResidual) {
+        residual_finish16<BM, BN, TM, TN, WTM, WN>(acc, Cout, M, N, m0, n0, wm, wn, lane, pid_n, rope);
+        return;
+    }
+    const float *inv = rope.row_ssq ? s_inv : nullptr;
+    const int n_lim = epi_paired(EPI) ? N / 2 : N;
+    if (m0 + BM <= M && n0 + BN_OUT <= n_lim && (n_lim & 3) == 0 && (N & 3) == 0)
+        store_tile16<TM, TN, WTM, EPI, false>(acc, Cout, M, N, m0, n0, wm, wn, lane, blockIdx.y, rope, inv);
+    else
+        store_tile16<TM, TN, WTM, EPI, true>(acc, Cout, M, N, m0, n0, wm, wn, lane, blockIdx.y, rope, inv);
+}
+
 // ---- fallback kernel: any K % 8 == 0 -------------------------------------------
 template <int BM, int BN, int WM, int WN, int EPI>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_reg_kernel(const uint16_t *__restrict__ A,
@@ -817,35 +1259,37 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_reg_kernel(const uint16_t *
 
 // ---- host side ----------------------------------------------------------------
 
-// Tile shapes with the modelled cost of one 64-deep K-step and of the epilogue in
-// microseconds when every CU holds a workgroup (measured on MI355X with random
-// operands; under that load the shader clock sits near 1.5 GHz; the three 256-row
-// tiles are fitted to many-round runs at M = 4096 and 12288 as well as to M = 512:
-// per round of 64 K-steps the 256x256 tile takes 115-120 us, 256x192 99-105 us,
-// 256x128 66-77 us, so the largest tile is the cheapest per flop once M fills it).
+// Tile shapes with the modelled cost of one 64-deep K-step and of a round's prologue and epilogue in microseconds
+// when every CU holds a workgroup.  step_us / epi_us were fitted (smallest mean loss of the planned choice against
+// the fastest one measured, 0.9 %) to all shapes at the five products of a d = 4096, f = 12288, V = 126464 layer,
+// 32 to 8192 rows, 1 to 8 K splits, random operands, panel-major: the chip is power limited and its clock sits near
+// 1.5 GHz there, so these are not cycle counts.
+// q: gemm_q_kernel.  gemm_il_kernel keeps the tiles it is the faster one at: 64-deep stages need half the barriers
+// per byte, which shows where a workgroup does little but stream weights (96 rows and fewer, and the O projection
+// with its 4096 columns: 512 rows, 128x128 tiles, 2 splits 22.0 vs 21.8 us, 32 rows 9.3 vs 10.6 us).
 struct TileCfg {
     int bm, bn, bk, nst, wn;  // wn: wave columns of the tile
     float step_us, epi_us;
+    bool q;
 };
-constexpr int kNumCfg = 10;
+constexpr int kNumCfg = 11;
 const TileCfg kCfg[kNumCfg] = {
-    {256, 256, 32, 4, 2, 1.70f, 9.0f}, {256, 192, 32, 5, 2, 1.45f, 8.0f}, {256, 128, 64, 3, 2, 0.97f, 6.0f},
-    {256, 96, 64, 3, 1, 0.77f, 5.0f},  {128, 128, 64, 4, 2, 0.62f, 3.5f}, {128, 64, 64, 4, 2, 1.00f, 2.5f},
-    {64, 64, 64, 8, 2, 0.30f, 1.5f},  // few rows (cached steps): a deep ring keeps 56 KB of weights in flight per workgroup
-    // 32-deep stages with deep rings: with panel-major operands a 64-byte row piece is as cheap a request as a
-    // 128-byte one, and the ring then looks further ahead in time
-    {128, 192, 32, 7, 2, 0.72f, 5.0f}, {256, 128, 32, 6, 2, 1.00f, 6.0f}, {128, 128, 32, 8, 2, 0.66f, 3.5f},
+    {256, 256, 32, 4, 2, 1.579f, 5.0f, true},  {256, 192, 32, 5, 2, 1.280f, 2.0f, true}, {256, 128, 32, 6, 2, 0.884f, 1.0f, true},
+    {160, 192, 32, 7, 2, 0.840f, 5.0f, true},  {128, 128, 64, 4, 2, 0.571f, 1.0f, false}, {128, 64, 64, 4, 2, 0.340f, 5.0f, false},
+    {64, 64, 64, 8, 2, 0.290f, 1.0f, false},  // few rows (cached steps): a deep ring keeps 56 KB of weights in flight per workgroup
+    {128, 192, 32, 7, 2, 0.780f, 1.0f, true},  {160, 128, 32, 8, 2, 0.640f, 2.0f, true}, {128, 128, 32, 8, 2, 0.604f, 1.0f, false},
+    {192, 256, 32, 5, 2, 1.171f, 5.0f, true},
 };
 constexpr int kNumCU = 256;
 constexpr int kLdsPerCU = 160 * 1024;
 // Weight streaming: a workgroup keeps (NST - 1) stages of its W tile in flight and a request takes about
-// 2 us under load, so few or shallow workgroups cannot pull the ~4.3 TB/s the HBM delivers to this pattern
-// (measured on the vocabulary projection at M = 256, where every workgroup streams a W tile of its own).
-constexpr double kHbmBytesPerUs = 4.3e6, kLoadLatencyUs = 2.0;
+// 2 us under load, so few or shallow workgroups cannot pull the ~6.4 TB/s the HBM delivers to this pattern
+// (measured on the vocabulary projection at 32 rows, where every workgroup streams a W tile of its own: 161 us).
+constexpr double kHbmBytesPerUs = 6.4e6, kLoadLatencyUs = 2.0;
 
 struct Plan {
     int cfg, splits;
-    bool fast;  // gemm_il_kernel
+    bool fast;  // asynchronous copies: gemm_q_kernel or gemm_il_kernel
 };
 
 // Test and tuning hooks from the environment, read once (and again by gemm_reload_env): DLLM_GEMM_FALLBACK
@@ -890,13 +1334,12 @@ EnvHooks env_hooks()
 }
 
 // epi: a GemmEpilogue value or one of the rotary epilogues
-bool cfg_allows(int c, int epi, bool fast)
+bool cfg_allows(int c, int epi, int splits, bool fast)
 {
-    if (!fast && c < 2) return false;  // the register-staged kernel keeps to the smaller tiles
-    // 256 accumulator registers per lane leave no room for the addresses of the fp32 epilogues (the residual
-    // epilogue compiles with 360 bytes of scratch per lane), and at N = 4096 it measured no faster than the
-    // 256x128 tile (B = 8, L = 1536: 162.4-162.6 ms per step either way)
-    if (c == 0 && (epi == kEpiPartial || epi == kEpiResidual)) return false;
+    // the register-staged kernel is built for the tiles whose waves hold whole 32x32 tiles in few registers
+    if (!fast && (c == 0 || c == 1 || c == 3 || c == 8 || c == 10)) return false;
+    // 256 accumulator registers per lane leave no room for the slab addresses of the fp32 epilogues
+    if (c == 0 && (epi == kEpiPartial || (epi == kEpiResidual && splits > 1))) return false;
     // a wave's slice of a row is at least 64 columns wide, which bounds the partial results per row
     if (epi == kEpiRowStats && kCfg[c].bn / kCfg[c].wn < 64) return false;
     return true;
@@ -917,15 +1360,13 @@ Plan search_plan(const EnvHooks &env, int epi, int M, int N, int K, int split_li
     const bool splittable = epi == kEpiPartial || epi == kEpiResidual;
     const int max_splits = splittable ? (split_limit < 1 ? 1 : split_limit > kGemmMaxSplits ? kGemmMaxSplits : split_limit) : 1;
     for (int c = 0; c < kNumCfg; ++c) {
-        if (!cfg_allows(c, epi, fast) || (fc >= 0 && fc < kNumCfg && cfg_allows(fc, epi, fast) && c != fc)) continue;
-        // a single row of 256x256 tiles that only streams W and writes bf16 logits measured 315 us where the model
-        // says 271 and the 256x128 tile takes 284 (row-major operands); with the row-statistics epilogue, panel-major
-        // weights and non-temporal copies the largest tile is the fastest (228 vs 250-257 us at 256 rows) and stays in
-        if (c == 0 && fc != 0 && M < 1024 && epi == kEpiBf16 && N > 16 * K) continue;
+        if (fc >= 0 && fc < kNumCfg && cfg_allows(fc, epi, 1, fast) && c != fc) continue;
         const TileCfg &t = kCfg[c];
         const int bn_out = epi == kEpiSwiglu ? t.bn / 2 : t.bn;
-        const long tiles = (long)((M + t.bm - 1) / t.bm) * ((n_out + bn_out - 1) / bn_out);
+        const int m_tiles = (M + t.bm - 1) / t.bm;
+        const long tiles = (long)m_tiles * ((n_out + bn_out - 1) / bn_out);
         for (int s = 1; s <= max_splits; ++s) {
+            if (!cfg_allows(c, epi, s, fast)) continue;
             if (fs >= 1 && fs <= max_splits && s != fs) continue;
             const int kps = ((K + s - 1) / s + 63) / 64 * 64;
             if (s > 1 && (long)kps * (s - 1) >= K) continue;  // the last split would be empty
@@ -933,9 +1374,8 @@ Plan search_plan(const EnvHooks &env, int epi, int M, int N, int K, int split_li
             const long rounds = (wgs + kNumCU - 1) / kNumCU;
             // a round that leaves CUs idle runs its workgroups faster (power and bandwidth are shared by fewer)
             const double fill = (double)wgs / (double)(rounds * kNumCU);
-            // sub-tiles without rows are skipped by the kernel
-            const int m_tiles = (M + t.bm - 1) / t.bm;
-            const double rows_frac = (double)((M + 31) / 32 * 32) / (double)(m_tiles * t.bm);
+            // gemm_il_kernel skips 32-row sub-tiles without rows
+            const double rows_frac = t.q ? 1.0 : (double)((M + 31) / 32 * 32) / (double)(m_tiles * t.bm);
             const double compute = (double)rounds * (double)(kps / 64) * t.step_us * (0.55 + 0.45 * fill) * rows_frac;
             const int per_cu = kLdsPerCU / (t.nst * (t.bm + t.bn) * t.bk * 2) >= 2 ? 2 : 1;
             const double in_flight = (double)(wgs < (long)kNumCU * per_cu ? wgs : (long)kNumCU * per_cu) *
@@ -944,7 +1384,9 @@ Plan search_plan(const EnvHooks &env, int epi, int M, int N, int K, int split_li
             const long cap = (long)kNumCU * per_cu;  // a partly filled last round streams at a lower rate
             const double stream = (double)N * K * 2.0 / bw * (wgs > cap ? (double)((wgs + cap - 1) / cap * cap) / (double)wgs : 1.0);
             double cost = (compute > stream ? compute : stream) + (double)rounds * (t.epi_us + 1.5);
-            if (splittable) cost += (double)s * M * N * 8.0 / 4.0e6;  // slab write + read, ~4 TB/s
+            // splits write fp32 slabs, and the launch that reads them back and normalises takes at least 6 us
+            // (10 bytes of residual stream and operand per element are moved by either form)
+            if (splittable && s > 1) cost += (double)s * M * N * 8.0 / 4.0e6 + 6.0;
             if (cost < best_cost) { best_cost = cost; best = Plan{c, s, fast}; }
         }
     }
@@ -983,36 +1425,51 @@ bool set_layout(RopeArgs &r, const GemmLayout &lay, bool fast, int K)
     return true;
 }
 
-template <int BM, int BN, int WM, int WN, int BK, int NST, int EPI>
-hipError_t launch_cfg(hipStream_t stream, bool fast, const void *A, const void *W, void *C, int M, int N, int K,
-                      int splits, RopeArgs rope)
+// Grid and dynamic LDS of a launch; the attribute is set once per kernel, whichever thread comes first
+// (initialisation of a local static is thread-safe).
+template <int BM, int BN, int EPI, class Kern>
+hipError_t launch_tiles(hipStream_t stream, Kern kern, hipError_t attr, int threads, size_t lds, const void *A, const void *W,
+                        void *C, int M, int N, int K, int splits, const RopeArgs &rope)
 {
+    if (attr != hipSuccess) return attr;
     constexpr int BN_OUT = epi_paired(EPI) ? BN / 2 : BN;
     const int n_lim = epi_paired(EPI) ? N / 2 : N;
     const int num_m = (M + BM - 1) / BM, num_n = (n_lim + BN_OUT - 1) / BN_OUT;
     const int kps = ((K + splits - 1) / splits + 63) / 64 * 64;
-    const dim3 grid(num_m * num_n, splits), block(WM * WN * 64);
-    if (fast) {
-        const size_t lds = (size_t)NST * (BM + BN) * BK * 2;
-        auto kern = gemm_il_kernel<BM, BN, WM, WN, BK, NST, EPI>;
-        // once per kernel, whichever thread comes first (initialisation of a local static is thread-safe)
-        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (attr != hipSuccess) return attr;
-        hipLaunchKernelGGL(kern, grid, block, lds, stream, (const uint16_t *)A, (const uint16_t *)W, C, M, N, K, kps,
-                           num_m, num_n, rope);
-    } else if constexpr (BM * BN > 256 * 128) {
-        return hipErrorInvalidValue;  // never planned: see cfg_allows
-    } else {
-        const size_t lds = (size_t)2 * (BM + BN) * 128;
-        auto kern = gemm_reg_kernel<BM, BN, WM, WN, EPI>;
-        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (attr != hipSuccess) return attr;
-        hipLaunchKernelGGL(kern, grid, block, lds, stream, (const uint16_t *)A, (const uint16_t *)W, C, M, N, K, kps,
-                           num_m, num_n, rope);
-    }
+    hipLaunchKernelGGL(kern, dim3(num_m * num_n, splits), dim3(threads), lds, stream, (const uint16_t *)A, (const uint16_t *)W, C,
+                       M, N, K, kps, num_m, num_n, rope);
     return hipGetLastError();
+}
+template <class Kern>
+hipError_t allow_lds(Kern kern, size_t lds)
+{
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+}
+
+// REG: the tile is also built as gemm_reg_kernel, for shapes the asynchronous copies do not take (see cfg_allows)
+template <int BM, int BN, int BK, int NST, bool Q, bool REG, int EPI>
+hipError_t launch_cfg(hipStream_t stream, bool fast, const void *A, const void *W, void *C, int M, int N, int K, int splits,
+                      const RopeArgs &rope)
+{
+    const size_t lds = fast ? (size_t)NST * (BM + BN) * BK * 2 : (size_t)2 * (BM + BN) * 128;
+    if (fast && Q) {
+        if constexpr (Q) {
+            auto kern = gemm_q_kernel<BM, BN, 2, 2, NST, EPI>;
+            static const hipError_t attr = allow_lds(kern, lds);
+            return launch_tiles<BM, BN, EPI>(stream, kern, attr, 256, lds, A, W, C, M, N, K, splits, rope);
+        }
+    } else if (fast) {
+        if constexpr (!Q) {
+            auto kern = gemm_il_kernel<BM, BN, 2, 2, BK, NST, EPI>;
+            static const hipError_t attr = allow_lds(kern, lds);
+            return launch_tiles<BM, BN, EPI>(stream, kern, attr, 256, lds, A, W, C, M, N, K, splits, rope);
+        }
+    } else if constexpr (REG) {
+        auto kern = gemm_reg_kernel<BM, BN, 2, 2, EPI>;
+        static const hipError_t attr = allow_lds(kern, lds);
+        return launch_tiles<BM, BN, EPI>(stream, kern, attr, 256, lds, A, W, C, M, N, K, splits, rope);
+    }
+    return hipErrorInvalidValue;  // never planned: see cfg_allows
 }
 
 template <int EPI>
@@ -1022,18 +1479,19 @@ hipError_t dispatch(hipStream_t stream, Plan p, const void *A, const void *W, vo
     if (!set_layout(rope, lay, p.fast, K)) return hipErrorInvalidValue;
     switch (p.cfg) {
     case 0:
-        if constexpr (EPI != kEpiPartial && EPI != kEpiResidual)
-            return launch_cfg<256, 256, 2, 2, 32, 4, EPI>(stream, p.fast, A, W, C, M, N, K, p.splits, rope);
+        if constexpr (EPI != kEpiPartial)
+            return launch_cfg<256, 256, 32, 4, true, false, EPI>(stream, p.fast, A, W, C, M, N, K, p.splits, rope);
         return hipErrorInvalidValue;  // never planned: see cfg_allows
-    case 1: return launch_cfg<256, 192, 2, 2, 32, 5, EPI>(stream, p.fast, A, W, C, M, N, K, p.splits, rope);
-    case 2: return launch_cfg<256, 128, 2, 2, 64, 3, EPI>(stream, p.fast, A, W, C, M, N, K, p.splits, rope);
-    case 3: return launch_cfg<256, 96, 4, 1, 64, 3, EPI>(stream, p.fast, A, W, C, M, N, K, p.splits, rope);
-    case 4: return launch_cfg<128, 128, 2, 2, 64, 4, EPI>(stream, p.fast, A, W, C, M, N, K, p.splits, rope);
-    case 5: return launch_cfg<128, 64, 2, 2, 64, 4, EPI>(stream, p.fast, A, W, C, M, N, K, p.splits, rope);
-    case 6: return launch_cfg<64, 64, 2, 2, 64, 8, EPI>(stream, p.fast, A, W, C, M, N, K, p.splits, rope);
-    case 7: return launch_cfg<128, 192, 2, 2, 32, 7, EPI>(stream, p.fast, A, W, C, M, N, K, p.splits, rope);
-    case 8: return launch_cfg<256, 128, 2, 2, 32, 6, EPI>(stream, p.fast, A, W, C, M, N, K, p.splits, rope);
-    default: return launch_cfg<128, 128, 2, 2, 32, 8, EPI>(stream, p.fast, A, W, C, M, N, K, p.splits, rope);
+    case 1: return launch_cfg<256, 192, 32, 5, true, false, EPI>(stream, p.fast, A, W, C, M, N, K, p.splits, rope);
+    case 2: return launch_cfg<256, 128, 32, 6, true, true, EPI>(stream, p.fast, A, W, C, M, N, K, p.splits, rope);
+    case 3: return launch_cfg<160, 192, 32, 7, true, false, EPI>(stream, p.fast, A, W, C, M, N, K, p.splits, rope);
+    case 4: return launch_cfg<128, 128, 64, 4, false, true, EPI>(stream, p.fast, A, W, C, M, N, K, p.splits, rope);
+    case 5: return launch_cfg<128, 64, 64, 4, false, true, EPI>(stream, p.fast, A, W, C, M, N, K, p.splits, rope);
+    case 6: return launch_cfg<64, 64, 64, 8, false, true, EPI>(stream, p.fast, A, W, C, M, N, K, p.splits, rope);
+    case 7: return launch_cfg<128, 192, 32, 7, true, true, EPI>(stream, p.fast, A, W, C, M, N, K, p.splits, rope);
+    case 8: return launch_cfg<160, 128, 32, 8, true, false, EPI>(stream, p.fast, A, W, C, M, N, K, p.splits, rope);
+    case 9: return launch_cfg<128, 128, 32, 8, false, true, EPI>(stream, p.fast, A, W, C, M, N, K, p.splits, rope);
+    default: return launch_cfg<192, 256, 32, 5, true, false, EPI>(stream, p.fast, A, W, C, M, N, K, p.splits, rope);
     }
 }
 

@@ -122,6 +122,22 @@ def test_linear_panel_major_operands(M, N, K, tile, a_pk, w_pk, monkeypatch):
                                           M + 37 if a_pk else 0, w_pk, 0), b.op_linear(Ad[21:21 + M].contiguous(), Wd))
 
 
+@pytest.mark.parametrize("tile", [0, 1, 2, 3, 7, 8, 10])
+@pytest.mark.parametrize("M,f,K", [(1, 16, 64), (33, 40, 128), (159, 200, 192), (161, 104, 320), (257, 300, 448), (193, 97, 704)])
+def test_16x16_tiles_at_their_edges(tile, M, f, K, monkeypatch):
+    """The tile shapes of the 16x16x32 kernel from panel-major operands, one row or column inside and outside a tile,
+    and reduction lengths of 2 to 22 stages around the 4 to 8 of the ring (odd rings copy one stage more in the tail)."""
+    monkeypatch.setenv("DLLM_GEMM_CFG", str(tile))
+    b = binding()                  # (re-reads the switch just set)
+    assert b.gemm_plan(0, M, 2 * f, K)["async_copy"] == 1
+    A = rand_bf16((M, K), 1.0, 31, f"A{M}{K}")
+    W = rand_bf16((2 * f, K), 0.08, 32, f"W{f}{K}")
+    Ap, Wp = b.op_pack_panels(A.to(DEV)).view(-1), b.op_pack_panels(W.to(DEV))
+    gu = oracle.linear(f64(A), bits(W))
+    close_bf16(f64(b.op_linear_panels(Ap, Wp, M, 2 * f, K, False, M, True, 0)), gu)
+    close_bf16(f64(b.op_linear_panels(Ap, Wp, M, 2 * f, K, True, M, True, 0)), oracle.swiglu(gu[:, :f], gu[:, f:]))
+
+
 @pytest.mark.parametrize("M,f,K", [(96, 704, 256), (130, 192, 128), (512, 1408, 512)])
 @pytest.mark.parametrize("tile", [-1, 0, 1, 2, 3, 4, 7, 8, 9])
 def test_linear_swiglu_panel_major_output(M, f, K, tile, monkeypatch):
@@ -334,6 +350,17 @@ def test_forward_tiny_config_every_tile_shape_of_the_fused_epilogues(epi, tile, 
         monkeypatch.setenv("DLLM_GEMM_FALLBACK", "1")
         got, ref = run_forward(cfg, 2)
         logits_close(got, ref)
+
+
+@pytest.mark.parametrize("epi", [1, 2, 3, 5, 6])
+def test_forward_tiny_config_192x256_tiles(epi, monkeypatch):
+    """The whole forward with one product family on the widest 16x16x32 tile, K splits of the slab epilogue included."""
+    monkeypatch.setenv(f"DLLM_GEMM_CFG_E{epi}", "10")
+    if epi == 2:
+        monkeypatch.setenv("DLLM_GEMM_SPLITS", "3")
+    cfg = dict(synth.CONFIGS["tiny"], d_ffn=704, prompt=100, gen=89)
+    got, ref = run_forward(cfg, 2)
+    logits_close(got, ref)
 
 
 def test_forward_tiny_config_wide_init_batch3():
