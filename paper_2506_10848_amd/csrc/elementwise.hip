@@ -120,6 +120,46 @@ __global__ __launch_bounds__(kThreads) void add_rmsnorm_kernel(float *__restrict
     }
 }
 
+// The same for rows of exactly 4 T elements: a thread holds its four in registers, so a row is one round of loads
+// (residual stream, slabs and gain together) and one reduction.  These launches are a chain of latencies, not of
+// bytes, where rows are few; the loop above reads its row a second time and the gain only then.
+template <int T>
+__global__ __launch_bounds__(T) void add_rmsnorm_row_kernel(float *__restrict__ x, const float *__restrict__ partials,
+                                                            int n_partials, size_t slab, const uint16_t *__restrict__ gain,
+                                                            uint16_t *__restrict__ h, float eps, int h_panel_rows)
+{
+    constexpr int d = 4 * T, kWaves = T / kWave, kMaxPartials = 8;
+    __shared__ float wsum[kWaves];
+    const int r = blockIdx.x, c = threadIdx.x;
+    float4 *xr = reinterpret_cast<float4 *>(x + (size_t)r * d);
+    float4 v = xr[c], p[kMaxPartials];
+#pragma unroll
+    for (int s = 0; s < kMaxPartials; ++s)
+        if (s < n_partials) p[s] = reinterpret_cast<const float4 *>(partials + s * slab + (size_t)r * d)[c];
+    const uint2 g = reinterpret_cast<const uint2 *>(gain)[c];
+#pragma unroll
+    for (int s = 0; s < kMaxPartials; ++s)
+        if (s < n_partials) { v.x += p[s].x; v.y += p[s].y; v.z += p[s].z; v.w += p[s].w; }
+    if (n_partials) xr[c] = v;
+    const float ss = wave_sum(v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w);
+    float tot = ss;
+    if constexpr (kWaves > 1) {
+        if ((c & (kWave - 1)) == 0) wsum[c / kWave] = ss;
+        __syncthreads();
+        tot = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) tot += wsum[w];
+    }
+    const float inv = rsqrtf(tot / (float)d + eps);
+    uint2 o;
+    o.x = pack_bf16x2(v.x * inv * bf16_lo(g.x), v.y * inv * bf16_hi(g.x));
+    o.y = pack_bf16x2(v.z * inv * bf16_lo(g.y), v.w * inv * bf16_hi(g.y));
+    if (h_panel_rows)  // elements 4c .. 4c+3 of row r: panel c / 8, 8-byte slot c % 8 of the row's 64 bytes
+        reinterpret_cast<uint2 *>(h)[((size_t)(c >> 3) * h_panel_rows + r) * 8 + (c & 7)] = o;
+    else
+        reinterpret_cast<uint2 *>(h + (size_t)r * d)[c] = o;
+}
+
 // (cos, sin) of pos * theta^(-2j/dh), evaluated in fp64.
 __device__ __forceinline__ float2 rope_angle(int pos, int j, int dh, float theta)
 {
@@ -199,8 +239,16 @@ hipError_t launch_add_rmsnorm(hipStream_t stream, float *x, const float *partial
                               void *h, int M, int d, float eps, int h_panel_rows)
 {
     if (h_panel_rows && (d % 32 || h_panel_rows < M)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(add_rmsnorm_kernel, dim3(M), dim3(kThreads), 0, stream, x, partials, n_partials,
-                       (size_t)M * d, (const uint16_t *)gain, (uint16_t *)h, d, eps, h_panel_rows);
+    const size_t slab = (size_t)M * d;
+    const uint16_t *g = (const uint16_t *)gain;
+    uint16_t *out = (uint16_t *)h;
+    // One thread per four elements where that is a workgroup of whole waves.  Rows of 4096: 32 rows 6.5 -> 4.9 us,
+    // 137 rows 6.9 -> 5.2, 288 rows 8.5 -> 7.9; at 512 rows both take 10.7 to 11.0 (bytes bound them) and at 768 the
+    // loop is ahead (13.0 against 15.0, sixteen waves wait at each row's barrier), so the line is drawn at 384.
+    if (d == 4096 && M <= 384) hipLaunchKernelGGL(add_rmsnorm_row_kernel<1024>, dim3(M), dim3(1024), 0, stream, x, partials, n_partials, slab, g, out, eps, h_panel_rows);
+    else if (d == 1024) hipLaunchKernelGGL(add_rmsnorm_row_kernel<256>, dim3(M), dim3(256), 0, stream, x, partials, n_partials, slab, g, out, eps, h_panel_rows);
+    else if (d == 256) hipLaunchKernelGGL(add_rmsnorm_row_kernel<64>, dim3(M), dim3(64), 0, stream, x, partials, n_partials, slab, g, out, eps, h_panel_rows);
+    else hipLaunchKernelGGL(add_rmsnorm_kernel, dim3(M), dim3(kThreads), 0, stream, x, partials, n_partials, slab, g, out, d, eps, h_panel_rows);
     return hipGetLastError();
 }
 

@@ -1261,8 +1261,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_reg_kernel(const uint16_t *
 
 // Tile shapes with the modelled cost of one 64-deep K-step and of a round's prologue and epilogue in microseconds
 // when every CU holds a workgroup.  step_us / epi_us were fitted (smallest mean loss of the planned choice against
-// the fastest one measured, 0.9 %) to all shapes at the five products of a d = 4096, f = 12288, V = 126464 layer,
-// 32 to 8192 rows, 1 to 8 K splits, random operands, panel-major: the chip is power limited and its clock sits near
+// the fastest one measured, 1.0 %) to all shapes at the products of a d = 4096, f = 12288, V = 126464 layer (32 to 8192
+// rows) and of a d = 1024, f = 2816 one (64 to 1536 rows), 1 to 8 K splits, random operands, panel-major: the chip is power limited and its clock sits near
 // 1.5 GHz there, so these are not cycle counts.
 // q: gemm_q_kernel.  gemm_il_kernel keeps the tiles it is the faster one at: 64-deep stages need half the barriers
 // per byte, which shows where a workgroup does little but stream weights (96 rows and fewer, and the O projection
@@ -1275,9 +1275,9 @@ struct TileCfg {
 constexpr int kNumCfg = 11;
 const TileCfg kCfg[kNumCfg] = {
     {256, 256, 32, 4, 2, 1.579f, 5.0f, true},  {256, 192, 32, 5, 2, 1.280f, 2.0f, true}, {256, 128, 32, 6, 2, 0.884f, 1.0f, true},
-    {160, 192, 32, 7, 2, 0.840f, 5.0f, true},  {128, 128, 64, 4, 2, 0.571f, 1.0f, false}, {128, 64, 64, 4, 2, 0.340f, 5.0f, false},
-    {64, 64, 64, 8, 2, 0.290f, 1.0f, false},  // few rows (cached steps): a deep ring keeps 56 KB of weights in flight per workgroup
-    {128, 192, 32, 7, 2, 0.780f, 1.0f, true},  {160, 128, 32, 8, 2, 0.640f, 2.0f, true}, {128, 128, 32, 8, 2, 0.604f, 1.0f, false},
+    {160, 192, 32, 7, 2, 0.840f, 5.0f, true},  {128, 128, 64, 4, 2, 0.548f, 1.0f, false}, {128, 64, 64, 4, 2, 0.320f, 3.0f, false},
+    {64, 64, 64, 8, 2, 0.300f, 1.0f, false},  // few rows (cached steps): a deep ring keeps 56 KB of weights in flight per workgroup
+    {128, 192, 32, 7, 2, 0.733f, 1.0f, true},  {160, 128, 32, 8, 2, 0.640f, 2.0f, true}, {128, 128, 32, 8, 2, 0.616f, 1.0f, false},
     {192, 256, 32, 5, 2, 1.171f, 5.0f, true},
 };
 constexpr int kNumCU = 256;
@@ -1372,11 +1372,14 @@ Plan search_plan(const EnvHooks &env, int epi, int M, int N, int K, int split_li
             if (s > 1 && (long)kps * (s - 1) >= K) continue;  // the last split would be empty
             const long wgs = tiles * s;
             const long rounds = (wgs + kNumCU - 1) / kNumCU;
-            // a round that leaves CUs idle runs its workgroups faster (power and bandwidth are shared by fewer)
+            // a round that leaves CUs idle runs its workgroups faster (power and bandwidth are shared by fewer), the
+            // small tiles less so: a stage of theirs is latency, not work (64x64, K = 2816: 14.3 us with 16 workgroups,
+            // 17.3 with 256); the register-staged kernel takes about twice as long for a stage
             const double fill = (double)wgs / (double)(rounds * kNumCU);
+            const double share = t.q ? 0.55 + 0.45 * fill : 0.8 + 0.2 * fill;
             // gemm_il_kernel skips 32-row sub-tiles without rows
             const double rows_frac = t.q ? 1.0 : (double)((M + 31) / 32 * 32) / (double)(m_tiles * t.bm);
-            const double compute = (double)rounds * (double)(kps / 64) * t.step_us * (0.55 + 0.45 * fill) * rows_frac;
+            const double compute = (double)rounds * (double)(kps / 64) * t.step_us * (fast ? 1.0 : 2.0) * share * rows_frac;
             const int per_cu = kLdsPerCU / (t.nst * (t.bm + t.bn) * t.bk * 2) >= 2 ? 2 : 1;
             const double in_flight = (double)(wgs < (long)kNumCU * per_cu ? wgs : (long)kNumCU * per_cu) *
                                      (double)((t.nst - 1) * t.bn * t.bk * 2);
@@ -1384,9 +1387,9 @@ Plan search_plan(const EnvHooks &env, int epi, int M, int N, int K, int split_li
             const long cap = (long)kNumCU * per_cu;  // a partly filled last round streams at a lower rate
             const double stream = (double)N * K * 2.0 / bw * (wgs > cap ? (double)((wgs + cap - 1) / cap * cap) / (double)wgs : 1.0);
             double cost = (compute > stream ? compute : stream) + (double)rounds * (t.epi_us + 1.5);
-            // splits write fp32 slabs, and the launch that reads them back and normalises takes at least 6 us
+            // splits write fp32 slabs, and the launch that reads them back and normalises takes at least 3 us
             // (10 bytes of residual stream and operand per element are moved by either form)
-            if (splittable && s > 1) cost += (double)s * M * N * 8.0 / 4.0e6 + 6.0;
+            if (splittable && s > 1) cost += (double)s * M * N * 8.0 / 4.0e6 + 3.0;
             if (cost < best_cost) { best_cost = cost; best = Plan{c, s, fast}; }
         }
     }

@@ -198,6 +198,22 @@ def test_add_rmsnorm(M, d, n):
     close_bf16(f64(h), oracle.rmsnorm(x_ref, bits(gain), 1e-5))
 
 
+@pytest.mark.parametrize("d,rows", [(256, (1, 96)), (1024, (1, 264)), (4096, (1, 384, 385))])
+def test_add_rmsnorm_one_thread_per_four_elements(d, rows):
+    """Row lengths with a workgroup of d / 4 threads, on both sides of the row count where 4096 goes back to the loop."""
+    b = binding()
+    for M in rows:
+        g = torch.Generator().manual_seed(M)
+        x, parts = torch.randn((M, d), generator=g), torch.randn((8, M, d), generator=g)
+        gain = rand_bf16((d,), 1.0, 41, "gain")
+        for n in (0, 1, 8):
+            xd = x.to(DEV)
+            h = b.op_add_rmsnorm(xd, parts[:n].contiguous().to(DEV) if n else None, gain.to(DEV), 1e-5)
+            x_ref = x.double().numpy() + parts[:n].double().numpy().sum(axis=0)
+            assert np.allclose(xd.cpu().double().numpy(), x_ref, rtol=1e-6, atol=2e-6)   # (up to eight fp32 additions)
+            close_bf16(f64(h), oracle.rmsnorm(x_ref, bits(gain), 1e-5))
+
+
 # ---- RoPE -----------------------------------------------------------------------
 
 @pytest.mark.parametrize("B,L,H,dh,theta", [(1, 96, 4, 64, 1e4), (2, 70, 3, 128, 5e5)])
