@@ -34,7 +34,8 @@ def step_flops(cfg, B, L, vocab_rows):
 
 def gemm_kernel_name(b, epi, M, N, K, what):
     p = b.gemm_plan(epi, M, N, K)
-    kern = "gemm_il_kernel" if p["async_copy"] else "gemm_reg_kernel"
+    # the planner's tiles of 128x192 and more are gemm_q_kernel's (16x16x32 products), the smaller ones gemm_il_kernel's
+    kern = "gemm_reg_kernel" if not p["async_copy"] else "gemm_q_kernel" if p["bm"] * p["bn"] > 128 * 128 else "gemm_il_kernel"
     return (f"{kern}<{p['bm']}x{p['bn']} tile, {p['waves_m']}x{p['waves_n']} waves, BK {p['bk']}, {p['stages']} stages, "
             f"{p['splits']} K split(s), {what}>")
 

@@ -1,24 +1,26 @@
 // bf16 MFMA GEMM for gfx950:  C = A[M][K] * W[N][K]^T, fp32 accumulation.
 //
-// Both operands are K-contiguous, which is what the 32x32x16 bf16 MFMA wants: a
+// Both operands are K-contiguous, which is what the bf16 MFMAs want: a
 // lane feeds 8 consecutive K values of one row (A) or one column (W).  A
-// workgroup of four waves (2x2 or 4x1, one wave per SIMD) owns a BM x BN tile
+// workgroup of four waves (2x2, one wave per SIMD) owns a BM x BN tile
 // and walks K in stages of BK = 32 or 64 through an LDS ring of NST stages.
 // Large wave tiles (up to 128x128) keep the LDS fragment traffic per flop low:
 // under MFMA load the chip is power limited (measured shader clocks of 1.4 to
 // 1.8 GHz), so bytes moved per flop decide the sustained rate as much as issue
 // slots do.
 //
-// Main kernel (gemm_il_kernel, K % 64 == 0):
+// Kernels, K % 64 == 0: gemm_q_kernel (16x16x32 products, fragments read a whole
+// stage ahead; the tiles of 256x128, 128x192 and more, see there) and
+// gemm_il_kernel (32x32x16; the smaller tiles), which share:
 //   * global -> LDS copies are asynchronous (global_load_lds_dwordx4, 1 KB per
 //     wave instruction, no VGPR staging) and run NST-1 stages ahead of the math.
 //   * One wave per SIMD means nothing else fills an issue bubble, so the stream
 //     is software-pipelined by hand: the fragment reads for the next K-substep
 //     and the copies of a later stage are spread one by one between the MFMAs
 //     of the current substep (an LDS read or copy issued right after an MFMA
-//     costs nothing, a clump of them stalls the matrix pipe), and the only
-//     barrier of a stage sits in front of the last substep's MFMAs, which hide
-//     it together with the first fragment reads of the next stage.
+//     costs nothing, a clump of them stalls the matrix pipe).  In gemm_il_kernel
+//     the only barrier of a stage sits in front of the last substep's MFMAs,
+//     which hide it together with the first fragment reads of the next stage.
 //   * The loop is split into a steady state (every step issues copies) and a
 //     tail (none left), so there is no branch between MFMAs; wait counts are
 //     compile-time constants in the steady state.
@@ -45,7 +47,7 @@
 // while they are copied: every 32-row MFMA tile holds 16 first partners (gate
 // rows; first half of a head) followed by their 16 second partners (up rows;
 // second half of the head), so both values of a pair end up in the same lane,
-// 8 accumulator elements apart, whatever the wave layout.
+// 8 accumulator elements (16x16 products: one tile) apart, whatever the wave layout.
 //
 // Workgroup ids are mapped so that the tiles sharing a weight column block run on
 // the same XCD (ids congruent mod 8 share an L2), and the workgroups of an XCD that
@@ -603,10 +605,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_il_kernel(const uint16_t *_
     // 32-row sub-tiles of this wave that hold at least one real row: the MFMAs of the others are
     // skipped (a ragged last M tile then costs its workgroups only the copies, and the chip is
     // power limited, so the cycles and the energy go to the tiles that have rows)
-    // (not in the 256x256 tile, whose 256 accumulator registers leave no room for one more value)
-    constexpr bool kSkipEmpty = BM * BN < 256 * 256;
     constexpr bool kEarlyReads = true;
-    const int tm_valid = kSkipEmpty ? __builtin_amdgcn_readfirstlane(min(TM, max(0, (M - m0 - wm * WTM + 31) / 32))) : TM;
+    const int tm_valid = __builtin_amdgcn_readfirstlane(min(TM, max(0, (M - m0 - wm * WTM + 31) / 32)));
     bf16x8 af[2][TM], bfr[2][TN];
     // fragments are read in the order of their first use by the MFMA sequence (i outer, j inner):
     // A0, W0 .. W(TN-1), A1 .. A(TM-1)
@@ -694,7 +694,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_il_kernel(const uint16_t *_
         }
     }
     };
-    if (kSkipEmpty && tm_valid < TM) k_loop(std::true_type{});
+    if (tm_valid < TM) k_loop(std::true_type{});
     else k_loop(std::false_type{});
 #undef DLLM_COPY
 #undef DLLM_READ
@@ -704,11 +704,9 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_il_kernel(const uint16_t *_
     }
     const float *inv = rope.row_ssq ? s_inv : nullptr;   // written before the K loop's barriers
     const int n_lim = epi_paired(EPI) ? N / 2 : N;
-    if constexpr (kSkipEmpty) {  // (the 256x256 tile has no register to spare for a second epilogue)
-        if (m0 + BM <= M && n0 + BN_OUT <= n_lim && (n_lim & 3) == 0 && (N & 3) == 0) {
-            store_tile<TM, TN, WTM, EPI, false>(acc, Cout, M, N, m0, n0, wm, wn, l32, lhalf, blockIdx.y, rope, inv);
-            return;
-        }
+    if (m0 + BM <= M && n0 + BN_OUT <= n_lim && (n_lim & 3) == 0 && (N & 3) == 0) {
+        store_tile<TM, TN, WTM, EPI, false>(acc, Cout, M, N, m0, n0, wm, wn, l32, lhalf, blockIdx.y, rope, inv);
+        return;
     }
     store_tile<TM, TN, WTM, EPI, true>(acc, Cout, M, N, m0, n0, wm, wn, l32, lhalf, blockIdx.y, rope, inv);
 }
